@@ -83,6 +83,31 @@ def test_lmhead_ragged_tiles(M, K, N, T):
           f"{same:.4f} equal to the rounded exact value, stats rel err {rel:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("M,K,N", [(5, 64, 50256), (33, 200, 50257), (65, 136, 50256),
+                                   (97, 8, 50257), (129, 72, 50256), (161, 200, 50257),
+                                   (193, 136, 50256), (256, 64, 50256), (450, 328, 50257),
+                                   (1040, 136, 50256)])
+def test_lmhead_tile_heights(M, K, N):
+    """Every tile height the launcher chooses (32 to 256 rows on 256 CUs), with
+    row tails, one and several rows of tiles, a last column tile of 80 or 81
+    columns, rows stored in vectors (N a multiple of 8) and element by
+    element, and one to six K slices, whole and ragged. Every logit against
+    the float64 product within the rounding bound of this file's head; the
+    statistics against those of the logits written (float32 terms: 1e-5)."""
+    g = torch.Generator(device=DEV).manual_seed(M + K)
+    x = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device=DEV) * (3.0 / K ** 0.5)).to(torch.bfloat16)
+    z, rm, rs = tv.lmhead_stats(x, w, 0.8)
+    exact = x.double() @ w.double().T
+    bound = x.double().abs() @ w.double().abs().T
+    zd = z.double()
+    assert torch.all((zd - exact).abs() <= 2.0 ** -8 * exact.abs() + 2.0 * K * 2.0 ** -24 * bound)
+    top = zd.amax(dim=-1)
+    assert torch.equal(rm.double(), top)
+    want = ((zd - top[:, None]) / float(np.float32(0.8))).exp().sum(dim=-1)
+    assert float(((rs - want).abs() / want).max()) < 1e-5
+
+
 def test_lmhead_rounding_is_nearest_even():
     """Integer inputs whose products and fp32 sums are exact (|sum| < 2^24),
     with sums of up to 13 significant bits: the bf16 rounding is then the only
