@@ -10,7 +10,10 @@
 // publishes the stripe's partial results and waits for the other members';
 // every member then combines the G partials in member order and continues.
 // The group only exchanges these partials, a few words per member and pass.
-// The launch is cooperative, so all members of a group are resident together.
+// A group begins once its members have all arrived (are resident), or, if other
+// work holds the device, with those that have arrived by then, so no workgroup
+// ever waits for one that is not running and an ordinary launch does (a
+// cooperative one costs 11 us before and 11 us after the kernel).
 // A group with no tree left lends its workgroups to running groups as
 // helpers: a helper takes stripes of another group's passes (the group's
 // member 0 publishes each batch for them), so the trees that run longest get
@@ -127,6 +130,7 @@ struct Params {
   int mode;
   int algo;
   int early;                 // skip updates that decide nothing (node_theta not asked for)
+  long long close_limit;     // wall-clock ticks a group waits for its members to arrive
   int G;                     // workgroups per group (per tree)
   int Gx;                    // most contributors (members + helpers) a group's pass has
   int ngroups;               // groups; group g verifies trees g, g + ngroups, ...
@@ -204,6 +208,21 @@ __device__ __forceinline__ SegPart* ws_parts(const PP& P, int g, int par, int p)
          ((static_cast<size_t>(g) * 2 + par) * kMaxBatch + p) * P.Gx;
 }
 
+// per group: 13 descriptor words, word 13 the arrivals, word 15 the helper count
+constexpr int kDescWords = 16;
+template <class PP>
+__device__ __forceinline__ uint64_t* ws_desc(const PP& P, int g) {
+  return reinterpret_cast<uint64_t*>(P.ws + P.off_desc) + static_cast<size_t>(g) * kDescWords;
+}
+template <class PP>
+__device__ __forceinline__ uint32_t* ws_arrive(const PP& P, int g) {
+  return reinterpret_cast<uint32_t*>(ws_desc(P, g) + 13);
+}
+template <class PP>
+__device__ __forceinline__ uint32_t* ws_hcount(const PP& P, int g) {
+  return reinterpret_cast<uint32_t*>(ws_desc(P, g) + 15);
+}
+
 __device__ __forceinline__ uint64_t ld_rlx(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -215,6 +234,44 @@ __device__ __forceinline__ void st_rlx(uint64_t* p, uint64_t v) {
 }
 __device__ __forceinline__ void st_rlx(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---------------------------------------------------------------------------
+// Arrival. A workgroup joins its group by counting up the group's arrival word
+// (bits 0-15); the count it found is its member number. The group has begun
+// when all G are there, or when member 0, having waited close_limit, closes it
+// with the members that are (kArriveClosed, their number in bits 16-30).
+// Everyone who waits here waits for member 0 at most, which is running; a
+// workgroup that arrives after the closing is no member and helps instead.
+// ---------------------------------------------------------------------------
+
+constexpr uint32_t kArriveClosed = 1u << 31;
+
+// Members of a group that has begun, 0 before.
+__device__ __forceinline__ int members_of(uint32_t word, int G) {
+  if (word & kArriveClosed) return static_cast<int>((word >> 16) & 0x7FFFu);
+  return static_cast<int>(word & 0xFFFFu) >= G ? G : 0;
+}
+
+// Thread 0, after joining (ws.joined) and a first look (ws.arrived): sets this
+// workgroup's rank and the group's members.
+template <class WS, class PP>
+__device__ __forceinline__ void enter_group(WS& ws, const PP& P, int g) {
+  const uint32_t joined = ws.joined;
+  ws.rank = joined & kArriveClosed ? -1 : static_cast<int>(joined & 0xFFFFu);
+  uint32_t word = ws.arrived;
+  const long long t0 = wall_clock64();
+  while (!members_of(word, P.G)) {
+    if (ws.rank == 0 && wall_clock64() - t0 >= P.close_limit) {
+      const uint32_t n = word & 0xFFFFu;
+      __hip_atomic_compare_exchange_strong(ws_arrive(P, g), &word, kArriveClosed | (n << 16) | n,
+                                           __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __builtin_amdgcn_s_sleep(1);
+    word = ld_rlx(ws_arrive(P, g));
+  }
+  ws.base = members_of(word, P.G);
 }
 
 // ---------------------------------------------------------------------------
@@ -318,6 +375,8 @@ struct WgScratch {
   double smp_window;        // mass of the window of chunks just scanned
   double smp_chunks[256];   // chunk sums of one window
   int hnext;                // helpers member 0 reported for the next batch
+  uint32_t joined, arrived; // the group's arrival word when this workgroup joined, and later
+  int rank, base;           // this workgroup's place in its group (-1: none), the group's members
   StripeResult res[kMaxBatch];   // this workgroup's results of the batch's passes
   uint64_t res_count;            // the count member 0 reports with them
   // a helper's view of the group it helps
@@ -1163,10 +1222,13 @@ __device__ __forceinline__ const T* row_ptr(const PP& P, const void* base, int b
 }
 
 // Loads and checks tree b into LDS, gathers every node's logits at its token
-// in its parent's rows, and starts the traversal (all threads).
+// in its parent's rows, and starts the traversal (all threads). With join >= 0
+// the workgroup also joins that group: the count and a first look at it travel
+// with the tree's own loads.
 template <typename T, class A, int kCap>
 __device__ __attribute__((noinline)) void begin_tree(Lds<TreeSmem<kCap>>& sm, Lds<WgScratch>& ws,
-                                                     const Lds<Params>& P, A ar, int b) {
+                                                     const Lds<Params>& P, A ar, int b,
+                                                     int join) {
   constexpr int kPer = (kCap + kNT - 1) / kNT;   // nodes per thread
   const int tid = threadIdx.x;
   const int n1 = P.num_nodes;
@@ -1179,6 +1241,10 @@ __device__ __attribute__((noinline)) void begin_tree(Lds<TreeSmem<kCap>>& sm, Ld
   // in the rows whatever the links; stored only once the tree is checked)
   int pr[kPer], xr[kPer];
   float ur[kPer], vb[kPer], vs[kPer];
+  uint32_t joined = 0, arrived = 0;
+  if (join >= 0 && tid == 0)
+    joined = __hip_atomic_fetch_add(ws_arrive(P, join), 1u, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
   for (int t = 0; t < kPer; ++t) {
     const int i = tid + t * kNT;
@@ -1216,6 +1282,7 @@ __device__ __attribute__((noinline)) void begin_tree(Lds<TreeSmem<kCap>>& sm, Ld
       sm.pini[i] = -1.0;
     }
   }
+  if (join >= 0 && tid == 0) arrived = ld_rlx(ws_arrive(P, join));
   bad_parent = __syncthreads_or(bad_parent);
   bad_token = __syncthreads_or(bad_token);
   if (tid == 0) {
@@ -1318,6 +1385,8 @@ __device__ __attribute__((noinline)) void begin_tree(Lds<TreeSmem<kCap>>& sm, Ld
     }
   }
   if (tid == 0) {
+    ws.joined = joined;
+    ws.arrived = arrived;
     sm.has_tree = 1;
     sm.tree = b;
     sm.cur = 0;
@@ -1555,7 +1624,7 @@ __device__ __attribute__((always_inline)) bool combine(Lds<TreeSmem<kCap>>& sm,
   if (ws.stop) return false;
   if (tid == 0) {
     sm.geff_last = G;
-    const int next = P.G + ws.hnext;
+    const int next = ws.base + ws.hnext;
     sm.geff = next > G ? next : G;
   }
   // children's original ratios r0 = p(x)/q(x) and draft terms: 32 threads per
@@ -1858,22 +1927,13 @@ __device__ __attribute__((noinline)) void controller_step(Lds<TreeSmem<kCap>>& s
 // group's passes like a member. Member 0 reads the count in every batch and
 // reports it (capped at Gx - G) in its partial of pass 0, so every member
 // agrees on the contributors of the next batch; the number only grows, and a
-// helper once counted works in every later batch of that group. While the
+// helper once counted works in every later batch of that group. Only a group
+// that has begun is helped: a helper waiting for one whose members are not
+// running could hold the place they need. While the
 // group has helpers, member 0 publishes each batch in a descriptor of 13
 // 64-bit words, each holding the batch number in its high half, so a helper
 // knows it read one whole descriptor when all 13 numbers agree.
 // ---------------------------------------------------------------------------
-
-constexpr int kDescWords = 16;     // per group: 13 descriptor words, word 15 the helper count
-
-template <class PP>
-__device__ __forceinline__ uint64_t* ws_desc(const PP& P, int g) {
-  return reinterpret_cast<uint64_t*>(P.ws + P.off_desc) + static_cast<size_t>(g) * kDescWords;
-}
-template <class PP>
-__device__ __forceinline__ uint32_t* ws_hcount(const PP& P, int g) {
-  return reinterpret_cast<uint32_t*>(ws_desc(P, g) + 15);
-}
 
 constexpr uint32_t kDescDone = 1u << 31;
 
@@ -2070,19 +2130,24 @@ template <typename T, class A, bool kShort>
 __device__ __forceinline__ void help_others(Lds<WgScratch>& ws, const Params& P, A ar,
                                             int g_self) {
   const int tid = threadIdx.x, lane = tid & 63;
-  const int cap = P.Gx - P.G;
   const int ng = P.ngroups;
+  // helpers of group gg if it runs and still takes one, else ~0
+  auto helpers = [&](int gg) -> uint32_t {
+    const uint64_t w0 = ld_rlx(&ws_desc(P, gg)[0]);
+    const uint32_t n = ld_rlx(ws_hcount(P, gg));
+    const int base = members_of(ld_rlx(ws_arrive(P, gg)), P.G);
+    const bool open = !(static_cast<uint32_t>(w0) & kDescDone) && base > 0 &&
+                      static_cast<int>(n) < P.Gx - base;
+    return open && gg != g_self ? n : ~0u;
+  };
   const uint32_t start = (static_cast<uint32_t>(blockIdx.x) * 2654435761u) % static_cast<uint32_t>(ng);
   for (;;) {
     if (tid < 64) {
       // fewest helpers among the running groups that take one
       uint32_t fewest = ~0u;
       for (int gg = lane; gg < ng; gg += 64) {
-        if (gg == g_self) continue;
-        const uint64_t w0 = ld_rlx(&ws_desc(P, gg)[0]);
-        if (static_cast<uint32_t>(w0) & kDescDone) continue;
-        const uint32_t n = ld_rlx(ws_hcount(P, gg));
-        if (static_cast<int>(n) < cap && n < fewest) fewest = n;
+        const uint32_t n = helpers(gg);
+        fewest = n < fewest ? n : fewest;
       }
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) {
@@ -2094,10 +2159,7 @@ __device__ __forceinline__ void help_others(Lds<WgScratch>& ws, const Params& P,
       if (fewest != ~0u) {
         for (int j = lane; j < ng; j += 64) {
           const int gg = static_cast<int>((start + static_cast<uint32_t>(j)) % static_cast<uint32_t>(ng));
-          if (gg == g_self) continue;
-          const uint64_t w0 = ld_rlx(&ws_desc(P, gg)[0]);
-          if (static_cast<uint32_t>(w0) & kDescDone) continue;
-          if (ld_rlx(ws_hcount(P, gg)) == fewest) {
+          if (helpers(gg) == fewest) {
             best = static_cast<uint32_t>(j);
             break;
           }
@@ -2112,9 +2174,10 @@ __device__ __forceinline__ void help_others(Lds<WgScratch>& ws, const Params& P,
         int g2 = best == ~0u ? -1 : static_cast<int>((start + best) % static_cast<uint32_t>(ng));
         int h = 0;
         if (g2 >= 0) {
+          const int base = members_of(ld_rlx(ws_arrive(P, g2)), P.G);
           h = static_cast<int>(__hip_atomic_fetch_add(ws_hcount(P, g2), 1u, __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT));
-          if (h >= cap) h = -1;          // taken meanwhile: look again
+          h = h < P.Gx - base ? base + h : -1;   // -1: taken meanwhile, look again
         }
         ws.help_g = g2;
         ws.help_h = h;
@@ -2125,7 +2188,7 @@ __device__ __forceinline__ void help_others(Lds<WgScratch>& ws, const Params& P,
     __syncthreads();
     if (g2 < 0) return;                  // no group takes a helper
     if (h < 0) continue;
-    if (!help_group<T, A, kShort>(ws, P, ar, g2, P.G + h)) return;
+    if (!help_group<T, A, kShort>(ws, P, ar, g2, h)) return;
   }
 }
 
@@ -2145,7 +2208,7 @@ __device__ __forceinline__ void run_batch(Lds<TreeSmem<kCap>>& sm, Lds<WgScratch
   // delaying them by a round trip.
   uint32_t hcount = 0;
   if (m == 0 && tid == 0) {
-    if (geff > P.G) publish_batch(P, g, seq, sm, geff);
+    if (geff > ws.base) publish_batch(P, g, seq, sm, geff);
     hcount = ld_rlx(ws_hcount(P, g));
   }
   const TermParams tp{sm.cmd_cb, sm.cmd_cs, sm.cmd_ap, sm.cmd_bp};
@@ -2164,7 +2227,7 @@ __device__ __forceinline__ void run_batch(Lds<TreeSmem<kCap>>& sm, Lds<WgScratch
     }
   }
   if (tid == 0) {
-    const int cap = P.Gx - P.G;
+    const int cap = P.Gx - ws.base;
     const int n = static_cast<int>(hcount);
     ws.res_count = m == 0 ? static_cast<uint64_t>(n < cap ? n : cap) : 0;
     // the partials are written by the next controller step
@@ -2228,17 +2291,25 @@ __global__ void __launch_bounds__(kNT) verify_kernel(Params P, A ar) {
   Lds<Params>& Ps = lds_ref(Ps_);
   const int tid = threadIdx.x;
   const int g = static_cast<int>(blockIdx.x) / P.G;
-  const int m = static_cast<int>(blockIdx.x) - g * P.G;
+  int m = -1;                // member number, given by the order of arrival
   if (tid == 0) {
     Ps_ = P;
     sm.seq = 0;
-    sm.geff = sm.geff_last = P.G;
     ws.stop = 0;
   }
   __syncthreads();
   bool live = true;
   for (int b = g; b < P.batch; b += P.ngroups) {
-    begin_tree<T>(sm, ws, Ps, ar, b);
+    begin_tree<T>(sm, ws, Ps, ar, b, b == g ? g : -1);
+    if (b == g) {
+      if (tid == 0) {
+        enter_group(ws, Ps, g);
+        sm.geff = sm.geff_last = ws.base;
+      }
+      __syncthreads();
+      m = ws.rank;
+      if (m < 0) break;      // the group began without this workgroup
+    }
     for (;;) {
       controller_step<T, A>(sm, ws, Ps, ar, g, m, false);
       while (sm.cmd == kCmdLocalSample) {
@@ -2263,7 +2334,8 @@ __global__ void __launch_bounds__(kNT) verify_kernel(Params P, A ar) {
   // for their loads one by one rather than for all at once
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   // the group has no tree left: help the groups that still run
-  if (P.Gx > P.G) help_others<T, A, (kCap > kCapSmall)>(ws, P, ar, g);
+  if (P.Gx > P.G || m < 0)
+    help_others<T, A, (kCap > kCapSmall)>(ws, P, ar, m < 0 ? -1 : g);
 }
 
 // Vocabularies below this use the precise element path whatever the dtype:
@@ -2339,6 +2411,11 @@ int launch_typed(Params P, A ar, hipStream_t stream) {
   if (gx < G) gx = G;
   P.Gx = static_cast<int>(gx);
   P.spin_limit = static_cast<long long>(clock_khz) * wait_limit_ms();
+  // a group's members arrive within a few us on an idle device
+  P.close_limit = static_cast<long long>(clock_khz) / 5;                     // 0.2 ms
+  // only what this launch uses is cleared
+  P.parts_words = static_cast<size_t>(ngroups) * 2 * kMaxBatch * P.Gx * (sizeof(SegPart) / 8);
+  P.desc_words = static_cast<size_t>(ngroups) * kDescWords;
   long long init_n = static_cast<long long>(P.parts_words);
   if (init_n < P.batch) init_n = P.batch;
   long long init_blocks = (init_n + 255) / 256;
@@ -2346,13 +2423,9 @@ int launch_typed(Params P, A ar, hipStream_t stream) {
   hipLaunchKernelGGL(init_kernel, dim3(static_cast<unsigned>(init_blocks)), dim3(256), 0, stream,
                      P);
   if (hipGetLastError() != hipSuccess) return TV_ERR_HIP;
-  // cooperative: the members of a group wait for each other, so all of them
-  // must be resident at once
-  void* args[] = {&P, &ar};
-  const hipError_t e = hipLaunchCooperativeKernel(
-      reinterpret_cast<const void*>(verify_kernel<T, A, kCap>),
-      dim3(static_cast<unsigned>(ngroups * G)), dim3(kNT), args, 0, stream);
-  return e == hipSuccess ? TV_OK : TV_ERR_HIP;
+  hipLaunchKernelGGL((verify_kernel<T, A, kCap>), dim3(static_cast<unsigned>(ngroups * G)),
+                     dim3(kNT), 0, stream, P, ar);
+  return hipGetLastError() == hipSuccess ? TV_OK : TV_ERR_HIP;
 }
 
 template <typename T, int kCap>

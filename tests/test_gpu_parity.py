@@ -342,6 +342,43 @@ def test_abandoned_launch_reports_sentinels(monkeypatch):
     assert_clean(rep, "call after an abandoned launch")
 
 
+@pytest.mark.parametrize("batch,vocab", [(256, 20000), (1, 128256)])
+def test_verify_beside_other_work(batch, vocab):
+    """Verifications on two streams while LM heads hold every CU's LDS on a
+    third: groups whose members cannot all run begin with those that do, and
+    workgroups that come later help. Every decision equals the undisturbed
+    call's (fewer members change only the sums' last bits); theta within the
+    near-tie band."""
+    bt = W.make_batch(5, step=31, device=DEV, mode=W.WITHOUT_REPLACEMENT, batch=batch,
+                      vocab=vocab)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    x = torch.randn((1024, 2048), generator=g, device=DEV).to(torch.bfloat16)
+    w = torch.randn((65536, 2048), generator=g, device=DEV).to(torch.bfloat16)
+
+    def verify():
+        return tv.verify_batch(bt["parents"], bt["tokens"], bt["target"], bt["draft"],
+                               bt["temperature"], bt["uniforms"], bt["mode"])
+    quiet = parity.host_outputs(verify())
+    assert (quiet["status"] == tv.TV_TREE_OK).all()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for _ in range(3):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(streams[0]):
+            keep = [tv.lmhead_stats(x, w, 1.0) for _ in range(3)]
+        outs = []
+        for s in streams[1:]:
+            with torch.cuda.stream(s):
+                outs += [verify(), verify()]
+        torch.cuda.synchronize()
+        del keep
+        for o in outs:
+            h = parity.host_outputs(o)
+            for k in ("status", "accept_len", "accepted_node", "bonus_token", "node_state",
+                      "counters"):
+                assert np.array_equal(h[k], quiet[k]), k
+            assert np.abs(h["node_theta"] - quiet["node_theta"]).max() < parity.BAND
+
+
 def test_batch_beyond_one_grid_of_trees():
     """300000 two-node trees (more trees than the initialisation grid has
     threads, so its per-tree loop strides): every tree verified, sampled trees
