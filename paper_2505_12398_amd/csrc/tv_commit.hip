@@ -9,46 +9,51 @@
 
 namespace {
 
-// One thread per tree. The chain is found by walking from the accepted node
-// to the root (each step to a smaller index, so at most num_nodes steps) and
-// written in reverse; entries past it are -1.
-__global__ void __launch_bounds__(256) commit_kernel(tv::CommitArgs a) {
-  const int b = static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x);
-  if (b >= a.batch) return;
+// One wavefront per tree, bound by latency: a few hundred bytes a tree, read
+// in one round of loads (links, status, accepted node and bonus token), then
+// the chain is found in LDS by walking from the accepted node to the root
+// (each step to a smaller index, so at most num_nodes steps) and its tokens
+// are gathered and everything is written by all lanes; entries past the chain
+// are -1. (One thread per tree, each step a
+// load of its own, took 7.5 us for 64 trees against 4.8 us, 4.2 of which any kernel takes.)
+constexpr int kWaves = 4;
+
+__global__ void __launch_bounds__(64 * kWaves) commit_kernel(tv::CommitArgs a) {
+  __shared__ int16_t link[kWaves][TV_MAX_NODES];   // parents, -1 where not smaller than the node
+  __shared__ int16_t chain[kWaves][TV_MAX_NODES];  // from the accepted node up
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b = static_cast<int>(blockIdx.x) * kWaves + wave;
+  const bool live = b < a.batch;
   const int n1 = a.num_nodes, L = a.max_len;
-  const int32_t* par = a.parents + static_cast<size_t>(b) * n1;
-  const int32_t* tok = a.tokens + static_cast<size_t>(b) * n1;
-  int32_t* pn = a.path_nodes + static_cast<size_t>(b) * L;
-  int32_t* pt = a.path_tokens + static_cast<size_t>(b) * (L + 1);
-  for (int i = 0; i < L; ++i) pn[i] = -1;
-  for (int i = 0; i <= L; ++i) pt[i] = -1;
-  if (a.status[b] != TV_TREE_OK) {
-    a.path_len[b] = 0;
-    return;
+  const size_t tree = static_cast<size_t>(live ? b : 0);
+  const int status = a.status[tree], acc = a.accepted_node[tree], bonus = a.bonus_token[tree];
+  for (int i = lane; i < n1; i += 64) {
+    const int p = a.parents[tree * n1 + i];
+    link[wave][i] = static_cast<int16_t>(p >= 0 && p < i ? p : -1);
   }
-  const int acc = a.accepted_node[b];
-  // depth of the accepted node; links must point backwards
-  int depth = 0, bad = acc < 0 || acc >= n1;
-  for (int x = acc; !bad && x > 0; ++depth) {
-    const int p = par[x];
-    if (p < 0 || p >= x) bad = 1;
-    x = p;
+  __syncthreads();
+  // length of the output, or the code of a tree that has none
+  int depth = 0, len = 0;
+  if (status == TV_TREE_OK) {
+    bool bad = acc < 0 || acc >= n1;
+    for (int x = acc; !bad && x > 0; ++depth) {
+      if (lane == 0) chain[wave][depth] = static_cast<int16_t>(x);
+      x = link[wave][x];
+      bad = x < 0;
+    }
+    len = bad ? TV_COMMIT_INCONSISTENT : depth > L ? TV_COMMIT_OVERFLOW : depth + 1;
   }
-  if (bad) {
-    a.path_len[b] = TV_COMMIT_INCONSISTENT;
-    return;
+  __syncthreads();
+  if (!live) return;
+  int32_t* pn = a.path_nodes + tree * L;
+  int32_t* pt = a.path_tokens + tree * (L + 1);
+  for (int i = lane; i <= L; i += 64) {
+    const bool in = len > 0 && i < depth;
+    const int x = in ? chain[wave][depth - 1 - i] : -1;
+    if (i < L) pn[i] = x;
+    pt[i] = in ? a.tokens[tree * n1 + x] : len > 0 && i == depth ? bonus : -1;
   }
-  if (depth > L) {
-    a.path_len[b] = TV_COMMIT_OVERFLOW;
-    return;
-  }
-  for (int x = acc, i = depth - 1; x > 0; --i) {
-    pn[i] = x;
-    pt[i] = tok[x];
-    x = par[x];
-  }
-  pt[depth] = a.bonus_token[b];
-  a.path_len[b] = depth + 1;
+  if (lane == 0) a.path_len[b] = len;
 }
 
 }  // namespace
@@ -56,8 +61,8 @@ __global__ void __launch_bounds__(256) commit_kernel(tv::CommitArgs a) {
 namespace tv {
 
 int launch_commit(const CommitArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(commit_kernel, dim3(static_cast<unsigned>((a.batch + 255) / 256)), dim3(256),
-                     0, stream, a);
+  hipLaunchKernelGGL(commit_kernel, dim3(static_cast<unsigned>((a.batch + kWaves - 1) / kWaves)),
+                     dim3(64 * kWaves), 0, stream, a);
   return hipGetLastError() == hipSuccess ? TV_OK : TV_ERR_HIP;
 }
 
