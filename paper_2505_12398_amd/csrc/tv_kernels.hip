@@ -388,16 +388,92 @@ struct WgScratch {
   double d_ap, d_bp, d_cb, d_cs;
 };
 
+// Reductions and scans over a wavefront's 64 lanes (all active) move values
+// with data-parallel primitives and row swaps, a few cycles a step; through LDS
+// permutes a step took about 100 cycles (8 deep trees 218 to 195 us, 32 binary
+// trees token-level 88 to 79, 256 trees 3%).
+enum : int {                // controls of the data-parallel primitives
+  kDppXor1 = 0xB1,          // quad_perm [1, 0, 3, 2]
+  kDppXor2 = 0x4E,          // quad_perm [2, 3, 0, 1]
+  kDppHalfMirror = 0x141,   // lane i of 8 reads 7 - i
+  kDppMirror = 0x140,       // lane i of 16 reads 15 - i
+  kDppShr = 0x110,          // + n: lane i of 16 reads i - n, 0 below
+  kDppBcast15 = 0x142,      // rows 1.. read the last lane of the row before
+  kDppBcast31 = 0x143       // rows 2, 3 read lane 31
+};
+template <int kCtrl, int kRows = 0xF>
+__device__ __forceinline__ double dpp(double v) {   // 0 where no lane is read
+  const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+      0, static_cast<int>(static_cast<uint32_t>(u)), kCtrl, kRows, 0xF, false));
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+      0, static_cast<int>(static_cast<uint32_t>(u >> 32)), kCtrl, kRows, 0xF, false));
+  return __longlong_as_double(
+      static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xF, 0xF, false));
+}
+
+// Both values of every pair of 16-lane rows (k32: of the two halves), in all
+// their lanes.
+template <bool k32>
+__device__ __forceinline__ void row_pair(uint32_t v, uint32_t& a, uint32_t& b) {
+  if constexpr (k32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+  }
+}
+template <bool k32>
+__device__ __forceinline__ double row_pair_sum(double v) {
+  const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+  uint32_t al, ah, bl, bh;
+  row_pair<k32>(static_cast<uint32_t>(u), al, bl);
+  row_pair<k32>(static_cast<uint32_t>(u >> 32), ah, bh);
+  return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(ah) << 32) | al)) +
+         __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(bh) << 32) | bl));
+}
+template <bool k32>
+__device__ __forceinline__ float row_pair_max(float v) {
+  uint32_t a, b;
+  row_pair<k32>(__float_as_uint(v), a, b);
+  return fmaxf(__uint_as_float(a), __uint_as_float(b));
+}
+
+// the sum / maximum of all lanes, in all lanes
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  v += dpp<kDppXor1>(v);
+  v += dpp<kDppXor2>(v);
+  v += dpp<kDppHalfMirror>(v);
+  v += dpp<kDppMirror>(v);
+  v = row_pair_sum<false>(v);
+  return row_pair_sum<true>(v);
 }
 
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
+  v = fmaxf(v, dpp<kDppXor1>(v));
+  v = fmaxf(v, dpp<kDppXor2>(v));
+  v = fmaxf(v, dpp<kDppHalfMirror>(v));
+  v = fmaxf(v, dpp<kDppMirror>(v));
+  v = row_pair_max<false>(v);
+  return row_pair_max<true>(v);
+}
+
+// inclusive sums in lane order
+__device__ __forceinline__ double wave_incl_scan(double v) {
+  v += dpp<kDppShr + 1>(v);
+  v += dpp<kDppShr + 2>(v);
+  v += dpp<kDppShr + 4>(v);
+  v += dpp<kDppShr + 8>(v);
+  v += dpp<kDppBcast15, 0xA>(v);
+  return v + dpp<kDppBcast31, 0xC>(v);
 }
 
 template <class WS>
@@ -446,12 +522,7 @@ __device__ __forceinline__ void block_max2(WS& ws, float& a, float& b) {
 template <class WS>
 __device__ __forceinline__ double block_incl_scan(WS& ws, double v) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const double o = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += o;
-  }
+  const double incl = wave_incl_scan(v);
   if (lane == 63) ws.scan_d[wave] = incl;
   __syncthreads();
   double base = 0.0;
@@ -1598,8 +1669,8 @@ __device__ __attribute__((always_inline)) bool combine(Lds<TreeSmem<kCap>>& sm,
       // stripe sums in the row's frame; a stripe with no finite value adds 0 (or NaN)
       double tb = (m0 > -INFINITY) ? s0 * exp2(Cb - ar.frame(m0)) : s0;
       double ts = two ? ((m1 > -INFINITY) ? s1 * exp2(Cs - ar.frame(m1)) : s1) : 0.0;
-      tb = __shfl(wave_sum(tb), 0, 64);
-      ts = __shfl(wave_sum(ts), 0, 64);
+      tb = wave_sum(tb);
+      ts = wave_sum(ts);
       if (lane == 0) {
         const bool bad = !(Mb > -INFINITY) || !isfinite(tb) ||
                          (two && (!(Ms > -INFINITY) || !isfinite(ts)));
@@ -1612,8 +1683,8 @@ __device__ __attribute__((always_inline)) bool combine(Lds<TreeSmem<kCap>>& sm,
         sm.flags[node] |= kFlagStats | (bad ? kFlagBad : 0);
       }
     } else {
-      const double S = __shfl(wave_sum(s0), 0, 64);
-      const double sd = __shfl(wave_sum(s1), 0, 64);
+      const double S = wave_sum(s0);
+      const double sd = wave_sum(s1);
       if (lane == 0) {
         sm.res_S = S;
         sm.res_sd = sd;
@@ -1672,12 +1743,7 @@ __device__ __attribute__((noinline)) void local_sample(Lds<TreeSmem<kCap>>& sm, 
         w = s0;
       }
     }
-    double incl = w;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const double o = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += o;
-    }
+    const double incl = wave_incl_scan(w);
     const double W = __shfl(incl, G - 1, 64);
     const double target = static_cast<double>(sm.u[0]) * W;
     const uint64_t pos = __ballot(lane < G && w > 0.0);
@@ -1774,12 +1840,7 @@ __device__ __attribute__((noinline)) void local_sample(Lds<TreeSmem<kCap>>& sm, 
           cs[j] = c < nck ? ws.smp_chunks[c] : 0.0;
           tot += cs[j];
         }
-        double incl = tot;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const double o = __shfl_up(incl, off, 64);
-          if (lane >= off) incl += o;
-        }
+        const double incl = wave_incl_scan(tot);
         double before = running + (incl - tot);
         int hit = -1, lastpos = -1;
         double hit_target = 0.0;
@@ -1822,12 +1883,7 @@ __device__ __attribute__((noinline)) void local_sample(Lds<TreeSmem<kCap>>& sm, 
       uint4 vb, vs;
       load_unit(i, vb, vs);
       const double us = unit_sum(i, vb, vs);
-      double incl = us;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += o;
-      }
+      const double incl = wave_incl_scan(us);
       const double tgt = fallback ? INFINITY : ws.smp_target;
       const uint64_t hits = __ballot(us > 0.0 && tgt < incl);
       const uint64_t poss = __ballot(us > 0.0);
@@ -2819,12 +2875,7 @@ __global__ void __launch_bounds__(kNT) sample_kernel(SampleParams S, A ar) {
         const int u = c * cu + lane;
         const bool mine = lane < cu && u < U;
         const double us = mine ? rw.unit_sum(u, cf) : 0.0;
-        double inc = us;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const double o = __shfl_up(inc, off, 64);
-          if (lane >= off) inc += o;
-        }
+        const double inc = wave_incl_scan(us);
         const double run = sm.run;
         const uint64_t pos = __ballot(us > 0.0);
         const uint64_t hitm = __ballot(mine && us > 0.0 && run + inc > target);
