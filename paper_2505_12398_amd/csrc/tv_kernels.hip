@@ -344,6 +344,34 @@ __device__ __forceinline__ SegRange stripe(const Geom& g, int m, int G) {
   return r;
 }
 
+// Contributor c's share of a batch of bn passes by G contributors: the passes p
+// with first <= p < last, stripe m of n of each. With at least two contributors
+// a pass the contributors are divided over the passes (each computes a wide
+// stripe of one pass), else over the rows (each computes a stripe of every
+// pass): a pass costs a contributor about 1.3 us of load latency and reductions
+// however narrow its stripe, so seven STATS passes by 31 contributors took
+// 13-17 us and now take 6 (one tree with commit 61 to 51 us, 16 trees with theta
+// 192 to 176, 8 deep trees 185 to 173, 64 chains 124 to 120). With fewer
+// contributors than that (a full device: 256 trees have three each) the passes
+// would not come out even, and the loads in flight hide that cost anyway.
+struct Share {
+  int first, last, m, n;
+};
+
+__device__ __forceinline__ Share share_of(int c, int G, int bn) {
+  // uniform across the workgroup
+  c = __builtin_amdgcn_readfirstlane(c);
+  G = __builtin_amdgcn_readfirstlane(G);
+  bn = __builtin_amdgcn_readfirstlane(bn);
+  if (bn == 1 || G < 2 * bn) return Share{0, bn, c, G};
+  const uint32_t g = static_cast<uint32_t>(G), n = static_cast<uint32_t>(bn);
+  // pass p is shared by contributors p G / bn .. (p + 1) G / bn - 1
+  const uint32_t p = ((static_cast<uint32_t>(c) + 1u) * n - 1u) / g;
+  const uint32_t lo = p * g / n, hi = (p + 1u) * g / n;
+  return Share{static_cast<int>(p), static_cast<int>(p) + 1, c - static_cast<int>(lo),
+               static_cast<int>(hi - lo)};
+}
+
 template <typename T>
 __device__ __forceinline__ uint4 load16(const T* row, int head, int v) {
   return *reinterpret_cast<const uint4*>(row + head + v * Elem<T>::E);
@@ -891,7 +919,7 @@ struct TreeSmem {
   int pending;
   uint32_t seq;                    // batches this group has run (all trees so far)
   int geff;                        // contributors (members + helpers) of the next batch
-  int geff_last;                   // contributors of the batch just completed
+  int geff_last;                   // contributors of pass 0 of the batch just completed
   int spass_node;                  // node whose SPASS partials are in the workspace (-1: none)
   double last_ap, last_bp, last_cb, last_cs;
   // local sample request
@@ -1694,7 +1722,7 @@ __device__ __attribute__((always_inline)) bool combine(Lds<TreeSmem<kCap>>& sm,
   __syncthreads();
   if (ws.stop) return false;
   if (tid == 0) {
-    sm.geff_last = G;
+    sm.geff_last = bn == 1 || G < 2 * bn ? G : G / bn;   // as share_of has it
     const int next = ws.base + ws.hnext;
     sm.geff = next > G ? next : G;
   }
@@ -1729,7 +1757,7 @@ __device__ __attribute__((noinline)) void local_sample(Lds<TreeSmem<kCap>>& sm, 
   constexpr int E = Elem<T>::E;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int node = sm.bnode[0];
-  const int G = sm.geff_last;           // contributors of the batch just completed
+  const int G = sm.geff_last;           // contributors of pass 0 of the batch just completed
   if (tid < 64) {
     const SegPart* part = ws_parts(P, g, static_cast<int>(sm.seq & 1u), 0);
     double w = 0.0;
@@ -2047,8 +2075,18 @@ __device__ __forceinline__ StripeResult stripe_pass(Lds<WgScratch>& ws, const T*
   return part;
 }
 
-// Thread 0: writes contributor c's partials of batch `seq` (pass p's result
-// for p < bn), together at the end of the batch, so that no store is in
+// The first lanes of wave 0, whose thread 0 writes the other results: an empty
+// one (no mass) for every pass of the batch the workgroup has no share in.
+__device__ __forceinline__ void empty_results(Lds<WgScratch>& ws, const Share& sh, int bn) {
+  const int p = threadIdx.x;
+  if (sh.last - sh.first != bn && p < bn && p != sh.first) {
+    ws.res[p].s0 = ws.res[p].s1 = 0.0;
+    ws.res[p].m0 = ws.res[p].m1 = -INFINITY;
+  }
+}
+
+// Thread 0: writes contributor c's partials of batch `seq` (its result of pass p
+// < bn, an empty one where it had no share), together at the end of the batch, so that no store is in
 // flight while the stripes run (the combine needs every pass anyway). One
 // entry p >= bn, chosen in turn, gets an empty partial, so that no entry is
 // more than 14 batches old: an entry left from an earlier batch never carries
@@ -2158,13 +2196,14 @@ __device__ __forceinline__ bool help_group(Lds<WgScratch>& ws, const Params& P, 
     last = seq;
     if (c < geff) {
       const TermParams tp{ws.d_cb, ws.d_cs, ws.d_ap, ws.d_bp};
-      for (int p = 0; p < bn; ++p) {
+      const Share sh = share_of(c, geff, bn);
+      for (int p = sh.first; p < sh.last; ++p) {
         const int node = ws.d_node[p];
         const T* rb = row_ptr<T>(P, P.target, tree, node);
         const T* rs = row_ptr<T>(P, P.draft, tree, node);
         const Geom geo = row_geom(rb, P.vocab);
-        const StripeResult part = stripe_pass<T, A, kShort>(ws, rb, rs, geo, stripe(geo, c, geff),
-                                                    ws.d_cmd[p], tp, ar);
+        const StripeResult part = stripe_pass<T, A, kShort>(
+            ws, rb, rs, geo, stripe(geo, sh.m, sh.n), ws.d_cmd[p], tp, ar);
         if (tid == 0) {
           ws.res[p].s0 = part.s0;
           ws.res[p].s1 = part.s1;
@@ -2172,6 +2211,7 @@ __device__ __forceinline__ bool help_group(Lds<WgScratch>& ws, const Params& P, 
           ws.res[p].m1 = part.m1;
         }
       }
+      empty_results(ws, sh, bn);
       if (tid == 0) write_parts(P, ws, g, seq, bn, c, 0);
     }
     __syncthreads();
@@ -2268,13 +2308,14 @@ __device__ __forceinline__ void run_batch(Lds<TreeSmem<kCap>>& sm, Lds<WgScratch
     hcount = ld_rlx(ws_hcount(P, g));
   }
   const TermParams tp{sm.cmd_cb, sm.cmd_cs, sm.cmd_ap, sm.cmd_bp};
-  for (int p = 0; p < bn; ++p) {
+  const Share sh = share_of(m, geff, bn);
+  for (int p = sh.first; p < sh.last; ++p) {
     const int node = sm.bnode[p];
     const T* rb = row_ptr<T>(P, P.target, b, node);
     const T* rs = row_ptr<T>(P, P.draft, b, node);
     const Geom geo = row_geom(rb, P.vocab);
     const StripeResult part = stripe_pass<T, A, (kCap > kCapSmall)>(
-        ws, rb, rs, geo, stripe(geo, m, geff), sm.bcmd[p], tp, ar);
+        ws, rb, rs, geo, stripe(geo, sh.m, sh.n), sm.bcmd[p], tp, ar);
     if (tid == 0) {
       ws.res[p].s0 = part.s0;
       ws.res[p].s1 = part.s1;
@@ -2282,6 +2323,7 @@ __device__ __forceinline__ void run_batch(Lds<TreeSmem<kCap>>& sm, Lds<WgScratch
       ws.res[p].m1 = part.m1;
     }
   }
+  empty_results(ws, sh, bn);
   if (tid == 0) {
     const int cap = P.Gx - ws.base;
     const int n = static_cast<int>(hcount);

@@ -342,6 +342,21 @@ def test_abandoned_launch_reports_sentinels(monkeypatch):
     assert_clean(rep, "call after an abandoned launch")
 
 
+@pytest.mark.parametrize("vocab", [20011, 32003, 61443, 65539])
+@pytest.mark.parametrize("theta", [True, False])
+def test_passes_divided_over_contributors(vocab, theta):
+    """Few trees: a batch of n passes is divided over the passes when the tree
+    has at least 2 n workgroups. One workgroup has at least 512 vectors, so the
+    vocabularies give 4, 7, 15 and 16 of them, and the irregular trees batches
+    of 1 to 8 passes (8 with the initial rates): on both sides of the rule, in
+    even and uneven parts, with heads and tails. Decisions, Y and counters equal
+    the oracle's; theta within the parity rule."""
+    for step, mode in ((41, W.WITHOUT_REPLACEMENT), (42, W.WITH_REPLACEMENT)):
+        bt = W.make_batch(5, step=step, device=DEV, mode=mode, batch=4, vocab=vocab)
+        rep = parity.check(bt, False, p_init=theta, theta=theta, label=f"V={vocab}")
+        assert_clean(rep, f"V={vocab} theta={theta} mode={mode}")
+
+
 @pytest.mark.parametrize("batch,vocab", [(256, 20000), (1, 128256)])
 def test_verify_beside_other_work(batch, vocab):
     """Verifications on two streams while LM heads hold every CU's LDS on a
