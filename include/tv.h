@@ -36,12 +36,13 @@
  * buffers or share a workspace must be ordered by the caller.
  *
  * Execution. One call enqueues a small initialisation kernel and one
- * cooperative launch of at most as many workgroups as the device holds at
+ * launch of at most as many workgroups as the device holds at
  * once, in groups that each verify one tree at a time (several workgroups per
  * tree; three per tree at 256 trees on MI355X). The members of a group
  * exchange partial sums through the workspace and wait for each other at
  * every vocabulary pass; a group with no tree left lends its workgroups to
- * running groups. The launch waits until the whole grid can be resident.
+ * running groups. A group begins when all its members run, or after 0.2 ms with
+ * those that do, so the launch needs no place for the whole grid.
  * Every wait inside the kernel is bounded: a call that makes no progress for
  * 4 seconds gives up and reports TV_TREE_ABORTED for the trees it did not
  * finish.

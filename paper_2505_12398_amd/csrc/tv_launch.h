@@ -163,7 +163,7 @@ int validate_sample(const SampleArgs& a);
 int launch_sample(const SampleArgs& a, hipStream_t stream);
 
 // Enqueue the verification on `stream` (an initialisation kernel, then the
-// cooperative verifier). Arguments already validated. Returns a tv_status_t.
+// verifier). Arguments already validated. Returns a tv_status_t.
 int launch(const VerifyArgs& a, Algo algo, void* workspace, hipStream_t stream);
 
 }  // namespace tv
