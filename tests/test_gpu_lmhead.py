@@ -108,6 +108,30 @@ def test_lmhead_tile_heights(M, K, N):
     assert float(((rs - want).abs() / want).max()) < 1e-5
 
 
+@pytest.mark.parametrize("T", [0.2, 0.05, 0.01, 0.001])
+@pytest.mark.parametrize("M,K,N", [(65, 72, 151936), (33, 64, 50257), (300, 72, 50256),
+                                   (450, 64, 50257)])
+def test_lmhead_sums_at_low_temperature(M, K, N, T):
+    """Row sums at the paper's lowest temperature and below it, down to the
+    lowest one taken, with one row of tiles (workgroups of three column tiles
+    and of one) and several. The frames (row maximum / T, up to 2^15 here) are
+    rounded, so partials may only be moved by the differences of the rounded
+    frames: the sums of the logits written are float32 terms summed in a few
+    levels, within 1e-6 whatever the temperature."""
+    g = torch.Generator(device=DEV).manual_seed(M + K)
+    x = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device=DEV) * (5.0 / K ** 0.5)).to(torch.bfloat16)
+    z, rm, rs = tv.lmhead_stats(x, w, T)
+    zd = z.double()
+    top = zd.amax(dim=-1)
+    assert float(top.max()) > 16.0
+    assert torch.equal(rm.double(), top)
+    want = ((zd - top[:, None]) / float(np.float32(T))).exp().sum(dim=-1)
+    rel = float(((rs - want).abs() / want).max())
+    print(f"lmhead M={M} N={N} T={T}: stats rel err {rel:.2e}", flush=True)
+    assert rel < 1e-6
+
+
 def test_lmhead_rounding_is_nearest_even():
     """Integer inputs whose products and fp32 sums are exact (|sum| < 2^24),
     with sums of up to 13 significant bits: the bf16 rounding is then the only
