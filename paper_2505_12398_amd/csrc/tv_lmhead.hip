@@ -33,7 +33,8 @@
 // even, by the hardware conversion); lanes exchange halves so that each stores
 // 16 bytes; each row's maximum and sum of 2^((z - max) k), k = log2(e)/T, in
 // fp32, are reduced over the four lanes and two wavefronts that hold the row:
-// one (max, sum) partial per row and column tile. A second kernel merges a
+// one (max, sum) partial per row and column tile (per column range where there
+// is one row of tiles, its tiles' sums added in fp64). A second kernel merges a
 // row's partials in fp64, each moved to the frame of the row maximum.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -84,7 +85,8 @@ struct LmParams {
 // up to 160 rows, which read the weight faster than they multiply, have three
 // or four (72 to 108 KB in flight per CU).
 constexpr int slice_bytes(int mb) { return (32 * mb + kBN) * kRowBytes; }
-constexpr int merge_bytes(int mb) { return 2 * 32 * mb * 8; }   // (max, sum) of the rows, twice
+// per row the right half's (max, sum), and a range's (max, fp64 sum) so far
+constexpr int merge_bytes(int mb) { return 32 * mb * (8 + 4 + 8); }
 constexpr int stages(int mb) {
   const int s = (kLdsBytes - merge_bytes(mb)) / slice_bytes(mb);
   return s < 4 ? s : 4;
@@ -204,6 +206,14 @@ __device__ __forceinline__ void merge_stats(float& m, float& s, float m2, float 
   const float f2 = m2 > -INFINITY ? __builtin_amdgcn_exp2f(c - -m2 * k) : 1.0f;
   s = s * f + s2 * f2;
   m = top;
+}
+
+// the sum s in the frame of m, moved to the frame of top >= m (as it is where
+// there is no finite value: 0 or NaN)
+__device__ __forceinline__ double moved(double s, float m, float top, float k) {
+  return m > -INFINITY
+             ? s * exp2(static_cast<double>(-top * k) - static_cast<double>(-m * k))
+             : s;
 }
 
 template <int MB, bool kRange, bool kOnce>
@@ -499,14 +509,28 @@ __global__ void __launch_bounds__(kThreads, 1) lmhead_kernel(LmParams P) {
             lds + merge + (wm * 16 * MB + 16 * a + er) * 8);
         float mx = acc[a][0][0], s = acc[a][0][1];
         merge_stats(mx, s, o[0], o[1], P.k32);
-        if constexpr (kRange) {       // those of the range so far, kept by this lane
-          auto* run = (__attribute__((address_space(3))) f32x2*)(
-              lds + merge + (32 * MB + wm * 16 * MB + 16 * a + er) * 8);
-          if (t > 0) {
-            const f32x2 before = *run;
-            merge_stats(mx, s, before[0], before[1], P.k32);
+        if constexpr (kRange) {
+          // those of the range so far, kept by this lane: the tiles' fp32 sums
+          // are added in fp64, as the merge kernel adds those of whole tiles
+          const int r = wm * 16 * MB + 16 * a + er;
+          auto* run_s = (__attribute__((address_space(3))) double*)(lds + merge + 32 * MB * 8 +
+                                                                    r * 8);
+          auto* run_m = (__attribute__((address_space(3))) float*)(lds + merge + 32 * MB * 16 +
+                                                                   r * 4);
+          if (ntiles > 1) {
+            double sum = static_cast<double>(s);
+            if (t > 0) {
+              const float m = *run_m;
+              const double before = *run_s;
+              const bool up = mx > m;   // the side with the smaller maximum moves
+              sum = (up ? sum : before) +
+                    moved(up ? before : sum, fminf(mx, m), fmaxf(mx, m), P.k32);
+              mx = fmaxf(mx, m);
+            }
+            *run_m = mx;
+            *run_s = sum;
+            s = static_cast<float>(sum);
           }
-          *run = f32x2{mx, s};
         }
         const int m = m0 + 16 * a + er;
         if (m < P.M && (!kRange || t + 1 == ntiles)) {

@@ -132,6 +132,32 @@ def test_lmhead_sums_at_low_temperature(M, K, N, T):
     assert rel < 1e-6
 
 
+def test_lmhead_range_sums_keep_their_precision():
+    """One row of tiles with sixteen column tiles a workgroup (V = 2^20 over 256
+    CUs): 256 equal logits of 0 in the first tile, whose terms sum to exactly
+    256, and one value z < 0 everywhere else, chosen so that a tile's sum
+    256 e^z lies 0.3 to 0.45 of an fp32 unit of 256 past a whole number of units.
+    Summed in fp32 every one of the fifteen further tiles loses that part,
+    together about 7e-7; in fp64 only the range's partial is rounded (2^-24),
+    and the terms' own error (2^-22 of the 0.5% that they add) is far below."""
+    N, K = 1 << 20, 8
+    z = torch.arange(-9.0, -6.0, 2.0 ** -4, dtype=torch.float64)   # bf16 values
+    frac = (256.0 * z.exp() * 2.0 ** 15).frac()
+    i = int((frac - 0.4).abs().argmin())
+    assert 0.3 < float(frac[i]) < 0.45
+    z = float(z[i])
+    x = torch.zeros((3, K), device=DEV, dtype=torch.bfloat16)
+    x[:, 0] = 1.0
+    w = torch.zeros((N // 4096, 4096, K), device=DEV, dtype=torch.bfloat16)
+    w[:, 256:, 0] = z
+    logits, rm, rs = tv.lmhead_stats(x, w.reshape(N, K), 1.0)
+    assert torch.all(rm == 0.0) and float(logits[0, 300]) == z
+    want = (N // 4096) * (256.0 + 3840.0 * float(np.exp(z)))
+    rel = float(((rs - want).abs() / want).max())
+    print(f"lmhead range sums: rel err {rel:.2e}", flush=True)
+    assert rel < 1e-7
+
+
 def test_lmhead_rounding_is_nearest_even():
     """Integer inputs whose products and fp32 sums are exact (|sum| < 2^24),
     with sums of up to 13 significant bits: the bf16 rounding is then the only
