@@ -2077,12 +2077,16 @@ __device__ __forceinline__ StripeResult stripe_pass(Lds<WgScratch>& ws, const T*
 
 // The first lanes of wave 0, whose thread 0 writes the other results: an empty
 // one (no mass) for every pass of the batch the workgroup has no share in.
+// Thread 0 reads them all in write_parts, a helper's without a barrier between:
+// the fence orders the lanes' stores before it (same wavefront, no instruction).
 __device__ __forceinline__ void empty_results(Lds<WgScratch>& ws, const Share& sh, int bn) {
   const int p = threadIdx.x;
   if (sh.last - sh.first != bn && p < bn && p != sh.first) {
     ws.res[p].s0 = ws.res[p].s1 = 0.0;
     ws.res[p].m0 = ws.res[p].m1 = -INFINITY;
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Thread 0: writes contributor c's partials of batch `seq` (its result of pass p

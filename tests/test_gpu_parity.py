@@ -357,6 +357,42 @@ def test_passes_divided_over_contributors(vocab, theta):
         assert_clean(rep, f"V={vocab} theta={theta} mode={mode}")
 
 
+def _group_words(ws, batch, word):
+    """One 64-bit word of every group's descriptor block in a workspace: 13 the
+    arrivals, 15 the helper count (tv_launch.h: a 256-byte header, the partials,
+    32 bytes x 2 parities x 8 passes a workgroup, then 128 bytes a group)."""
+    parts = 32 * 2 * 8 * min(batch * 64, 4096)
+    off = (256 + parts + 255) // 256 * 256
+    return ws[off:off + 128 * batch].view(torch.int64).view(batch, 16)[:, word].cpu().numpy()
+
+
+@pytest.mark.parametrize("theta", [True, False])
+def test_helpers_in_divided_batches(theta):
+    """Four valid trees among sixty whose links are invalid and whose groups end
+    at once: their workgroups help (12 members and up to 19 helpers a tree at
+    V = 128256), so batches of up to 8 passes are divided over members and
+    helpers, and a helper writes its own pass's results and empty ones for the
+    others. The helper counts show that every valid tree was helped."""
+    keep = [0, 21, 42, 63]
+    bt = W.make_batch(5, step=43, device=DEV, mode=W.WITHOUT_REPLACEMENT, batch=64)
+    bad = torch.ones(64, dtype=torch.bool, device=DEV)
+    bad[keep] = False
+    bt["parents"][bad, 1] = 5
+    ws, _ = tv.workspace_tensor(64, bt["parents"].shape[1], bt["target"].shape[-1], DEV)
+    for _ in range(3):
+        out = tv.verify_batch(bt["parents"], bt["tokens"], bt["target"], bt["draft"],
+                              bt["temperature"], bt["uniforms"], bt["mode"], want_p_init=theta,
+                              want_theta=theta, workspace=ws)
+        g = parity.host_outputs(out)
+        helpers = _group_words(ws, 64, 15)
+        print(f"helpers: {helpers[keep].tolist()}", flush=True)
+        assert (g["status"][bad.cpu().numpy()] == tv.TV_TREE_BAD_PARENT).all()
+        assert (helpers[keep] > 0).all()
+        rep = parity.check(bt, False, trees=keep, gpu=g, p_init=theta, theta=theta,
+                           label="helped")
+        assert_clean(rep, f"helpers in divided batches theta={theta}")
+
+
 @pytest.mark.parametrize("batch,vocab", [(256, 20000), (1, 128256)])
 def test_verify_beside_other_work(batch, vocab):
     """Verifications on two streams while LM heads hold every CU's LDS on a
