@@ -595,18 +595,26 @@ __global__ void __launch_bounds__(kThreads) lmhead_merge_kernel(LmParams P) {
 // the larger one, which reads the weight less often). 1040 rows at V = 128256:
 // five tiles of 224 rows instead of 256; 200 rows at V = 32000: four of 64,
 // which fill the CUs that one of 224 would leave idle.
-int tile_height(int rows, int tiles_n, int cus) {
+// With rows of more than 24 KB the slices of the tiles in flight outgrow the
+// caches, and a lower tile saves less than that: 256 rows there unless another
+// height is 1/16 cheaper (256 against 224 rows, us: 4000 x 16384 x 70001 7282,
+// 7961; x 14336 6156, 6516; x 12288 5330, 5388; 1040 x 16384 x 128256, 12%
+// cheaper with 224, 3873, 3780).
+constexpr int kLongRow = 12288;
+int tile_height(int rows, int tiles_n, int hidden, int cus) {
   int best = 1;
-  long long best_cost = -1;
+  long long best_cost = -1, tall_cost = 0;
   for (int mb = 8; mb >= 1; --mb) {
     const long long tiles = static_cast<long long>((rows + 32 * mb - 1) / (32 * mb)) * tiles_n;
     const long long rounds = (tiles + cus - 1) / cus;
     const long long cost = rounds * (256 * mb + 40 * (mb + kNB));
+    if (mb == 8) tall_cost = cost;
     if (best_cost < 0 || cost < best_cost) {
       best_cost = cost;
       best = mb;
     }
   }
+  if (hidden > kLongRow && 17 * best_cost > 16 * tall_cost) best = 8;
   return best;
 }
 
@@ -676,7 +684,7 @@ int launch_lmhead(const LmheadArgs& a, void* workspace, hipStream_t stream) {
   const int cus = device_cus();
   if (!cus) return TV_ERR_HIP;
   hipError_t e = hipErrorInvalidValue;
-  switch (tile_height(a.rows, L.tiles_n, cus)) {
+  switch (tile_height(a.rows, L.tiles_n, a.hidden_size, cus)) {
     case 1: e = run_tiles<1>(P, cus, stream); break;
     case 2: e = run_tiles<2>(P, cus, stream); break;
     case 3: e = run_tiles<3>(P, cus, stream); break;
