@@ -1,6 +1,8 @@
 """HIP verifiers against the CPU oracle on the same seeded inputs (needs an
 MI355X). Every call goes through the C-ABI library via its ctypes binding."""
 
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -391,6 +393,61 @@ def test_helpers_in_divided_batches(theta):
         rep = parity.check(bt, False, trees=keep, gpu=g, p_init=theta, theta=theta,
                            label="helped")
         assert_clean(rep, f"helpers in divided batches theta={theta}")
+
+
+@pytest.mark.parametrize("batch,vocab,held,deep", [
+    (1, 128256, 250, False), (4, 65539, 250, False), (64, 128256, 200, False),
+    (256, 32003, 200, False), (5, 50257, 226, True)])
+def test_groups_that_begin_short(batch, vocab, held, deep):
+    """Verification while LM heads of one row of tiles hold `held` of the CUs
+    for a few milliseconds (a workgroup of theirs leaves no room in its CU's
+    LDS): some groups cannot have all their members, begin after 0.2 ms
+    with those that run, and the workgroups that come later are no members.
+    With room for helpers beyond the full group (64 and 256 trees) and
+    without, in both sizes of the kernel. The arrival words show that groups
+    began short and that their latecomers came; with many trees, workgroups
+    whose own groups ended first have helped such groups. Four streams in
+    turn, as one of them may share the LM heads' hardware queue and wait for
+    them. Decisions, Y and counters equal the oracle's."""
+    if deep:
+        bt = W.make_deep_batch(batch=batch, vocab=vocab, step=3, device=DEV)
+    else:
+        bt = W.make_batch(5, step=44, device=DEV, mode=W.WITHOUT_REPLACEMENT, batch=batch,
+                          vocab=vocab)
+    trees = sorted({0, 1, batch // 3, batch // 2, batch - 2, batch - 1} & set(range(batch)))
+    refs = parity.oracle_many(bt, trees, tokenlevels=(False,))[False]
+    ws, _ = tv.workspace_tensor(batch, bt["parents"].shape[1], vocab, DEV)
+    x = torch.zeros((32, 65536), dtype=torch.bfloat16, device=DEV)
+    w = torch.zeros((256 * held, 65536), dtype=torch.bfloat16, device=DEV)
+    args = (bt["parents"], bt["tokens"], bt["target"], bt["draft"], bt["temperature"],
+            bt["uniforms"], bt["mode"])
+    outs = [tv.verify_batch(*args, want_theta=theta, workspace=ws) for theta in (True, False)]
+    tv.lmhead_stats(x, w, 1.0)
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    short = helped = 0
+    for it in range(8):
+        theta, stream, out = it % 2 == 0, streams[it // 2], outs[it % 2]
+        torch.cuda.synchronize()
+        keep = [tv.lmhead_stats(x, w, 1.0) for _ in range(3)]
+        time.sleep(1e-4)                   # the LM heads run
+        with torch.cuda.stream(stream):
+            tv.verify_batch(*args, out=out, workspace=ws)
+        torch.cuda.synchronize()
+        del keep
+        g = parity.host_outputs(out)
+        word = _group_words(ws, batch, 13) & 0xFFFFFFFF
+        closed = word >> 31 == 1
+        members, arrived = word >> 16 & 0x7FFF, word & 0xFFFF
+        assert (members[closed] >= 1).all() and (members[closed] < arrived[closed]).all()
+        assert (arrived == arrived[0]).all()
+        short += int(closed.sum())
+        helped += int((_group_words(ws, batch, 15)[closed] > 0).sum())
+        assert (g["status"] == tv.TV_TREE_OK).all()
+        rep = parity.check(bt, False, trees=trees, gpu=g, theta=theta, refs=refs, label="short")
+        assert_clean(rep, f"groups begun short: {int(closed.sum())} of {batch}, members "
+                          f"{members[closed][:8].tolist()} of {int(arrived[0])}")
+    print(f"{short} groups begun short, {helped} of them helped", flush=True)
+    assert short > 0 and (helped > 0 or batch < 64)
 
 
 @pytest.mark.parametrize("batch,vocab", [(256, 20000), (1, 128256)])
