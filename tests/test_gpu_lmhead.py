@@ -88,12 +88,37 @@ def test_lmhead_ragged_tiles(M, K, N, T):
                                    (193, 136, 50256), (256, 64, 50256), (450, 328, 50257),
                                    (1040, 136, 50256)])
 def test_lmhead_tile_heights(M, K, N):
-    """Every tile height the launcher chooses (32 to 256 rows on 256 CUs), with
-    row tails, one and several rows of tiles, a last column tile of 80 or 81
-    columns, rows stored in vectors (N a multiple of 8) and element by
-    element, and one to six K slices, whole and ragged. Every logit against
-    the float64 product within the rounding bound of this file's head; the
-    statistics against those of the logits written (float32 terms: 1e-5)."""
+    """Every tile height the launcher chooses (32 to 256 rows on 256 CUs) with one
+    row of tiles and one tile a workgroup, and two heights with several rows of
+    tiles; row tails, a last column tile of 80 or 81 columns, rows stored in
+    vectors (N a multiple of 8) and element by element, and one to six K
+    slices, whole and ragged. Every logit against the float64 product within
+    the rounding bound of this file's head; the statistics against those of
+    the logits written (float32 terms: 1e-5)."""
+    _check_lmhead(M, K, N, 1e-5)
+
+
+# on 256 CUs; the heights in units of 32 rows from left to right
+@pytest.mark.parametrize("M,K,N", [
+    # several rows of tiles at the other heights: 1, 2, 4, 5, 6, 8
+    (40, 72, 5000), (113, 200, 70001), (577, 72, 50256), (257, 200, 50257), (353, 136, 50256),
+    (500, 328, 50257),
+    # one row of tiles, two or three (151936, 184320) column tiles a workgroup: 1 to 8
+    (17, 72, 151936), (63, 200, 128257), (65, 136, 65537), (113, 72, 128256), (129, 8, 184321),
+    (177, 200, 128256), (209, 72, 151936), (241, 136, 128257),
+    # the same with a weight of more than 256 MiB, which is read past the caches: 1 to 8
+    (5, 1096, 128257), (33, 1096, 128256), (65, 1096, 128257), (97, 1096, 128256),
+    (129, 904, 151936), (161, 1096, 128256), (193, 1096, 128257), (225, 904, 184320)])
+def test_lmhead_kernel_variants(M, K, N):
+    """Every other variant of the kernel: several rows of tiles, and column
+    ranges of several tiles (from tile to tile the loads run on and the rows'
+    statistics are carried), from the caches and past them, each at every tile
+    height; ragged rows, columns and K. Logits as above; statistics of the
+    logits written within 1e-6 (float32 terms, few levels of sums)."""
+    _check_lmhead(M, K, N, 1e-6)
+
+
+def _check_lmhead(M, K, N, bound_sums):
     g = torch.Generator(device=DEV).manual_seed(M + K)
     x = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
     w = (torch.randn((N, K), generator=g, device=DEV) * (3.0 / K ** 0.5)).to(torch.bfloat16)
@@ -105,7 +130,7 @@ def test_lmhead_tile_heights(M, K, N):
     top = zd.amax(dim=-1)
     assert torch.equal(rm.double(), top)
     want = ((zd - top[:, None]) / float(np.float32(0.8))).exp().sum(dim=-1)
-    assert float(((rs - want).abs() / want).max()) < 1e-5
+    assert float(((rs - want).abs() / want).max()) < bound_sums
 
 
 @pytest.mark.parametrize("T", [0.2, 0.05, 0.01, 0.001])
