@@ -6,9 +6,10 @@
 // small for large ones). Every member of a group holds the tree in LDS and runs
 // the same sequential traversal on its thread 0, on the same data, so all
 // members take the same decisions. Whenever the traversal needs vocabulary-wide
-// quantities, each member computes its fixed 1/G stripe of the rows involved,
-// publishes the stripe's partial results and waits for the other members';
-// every member then combines the G partials in member order and continues.
+// quantities, each member computes a fixed stripe of the rows involved (with
+// many members of one row pair's rows only, share_of), publishes the stripes'
+// partial results and waits for the other members'; every member then combines
+// the partials in member order and continues.
 // The group only exchanges these partials, a few words per member and pass.
 // A group begins once its members have all arrived (are resident), or, if other
 // work holds the device, with those that have arrived by then, so no workgroup
@@ -17,8 +18,9 @@
 // A group with no tree left lends its workgroups to running groups as
 // helpers: a helper takes stripes of another group's passes (the group's
 // member 0 publishes each batch for them), so the trees that run longest get
-// more workgroups as the others finish. With helpers the number of stripes
-// of a pass depends on timing, and so do the last bits of the sums.
+// more workgroups as the others finish. With helpers, or in a group that began
+// with fewer members, the number of stripes of a pass depends on timing, and so
+// do the last bits of the sums.
 //
 // Pass kinds:
 //   STATS   per row: maximum and sum of 2^(z*k - max*k), k = log2(e)/T, over
@@ -350,8 +352,10 @@ __device__ __forceinline__ SegRange stripe(const Geom& g, int m, int G) {
 // stripe of one pass), else over the rows (each computes a stripe of every
 // pass): a pass costs a contributor about 1.3 us of load latency and reductions
 // however narrow its stripe, so seven STATS passes by 31 contributors took
-// 13-17 us and now take 6 (one tree with commit 61 to 51 us, 16 trees with theta
-// 192 to 176, 8 deep trees 185 to 173, 64 chains 124 to 120). With fewer
+// 13-17 us and now take 6 (without and with this rule on one card, us: one tree
+// with commit 110 and 98, 16 trees with theta 215 and 198, 8 deep trees 148 and
+// 139, 64 chains 123 and 119; the rule itself costs 32 token-level trees, whose
+// batches have one pass, 82 and 83). With fewer
 // contributors than that (a full device: 256 trees have three each) the passes
 // would not come out even, and the loads in flight hide that cost anyway.
 struct Share {
@@ -418,8 +422,9 @@ struct WgScratch {
 
 // Reductions and scans over a wavefront's 64 lanes (all active) move values
 // with data-parallel primitives and row swaps, a few cycles a step; through LDS
-// permutes a step took about 100 cycles (8 deep trees 218 to 195 us, 32 binary
-// trees token-level 88 to 79, 256 trees 3%).
+// permutes a step took about 100 cycles (through LDS and so on one card, us: 8
+// deep trees 191 and 181, 16 trees with theta 175 and 166, 32 binary trees
+// token-level 87 and 83, 256 trees 457 and 454, two trees' drafting 43 and 41).
 enum : int {                // controls of the data-parallel primitives
   kDppXor1 = 0xB1,          // quad_perm [1, 0, 3, 2]
   kDppXor2 = 0x4E,          // quad_perm [2, 3, 0, 1]
@@ -2006,10 +2011,11 @@ __device__ __attribute__((noinline)) void controller_step(Lds<TreeSmem<kCap>>& s
 }
 
 // ---------------------------------------------------------------------------
-// Helpers. A workgroup whose group has no tree left helps a running group: it
-// takes a number in the group's helper count and then computes stripes of the
-// group's passes like a member. Member 0 reads the count in every batch and
-// reports it (capped at Gx - G) in its partial of pass 0, so every member
+// Helpers. A workgroup whose group has no tree left, or began without it, helps
+// a running group: it takes a number in the group's helper count and then
+// computes stripes of the group's passes like a member. Member 0 reads the
+// count in every batch and reports it (capped so that members and helpers are
+// at most Gx) in its partial of pass 0, so every member
 // agrees on the contributors of the next batch; the number only grows, and a
 // helper once counted works in every later batch of that group. Only a group
 // that has begun is helped: a helper waiting for one whose members are not
@@ -2090,11 +2096,11 @@ __device__ __forceinline__ void empty_results(Lds<WgScratch>& ws, const Share& s
 }
 
 // Thread 0: writes contributor c's partials of batch `seq` (its result of pass p
-// < bn, an empty one where it had no share), together at the end of the batch, so that no store is in
-// flight while the stripes run (the combine needs every pass anyway). One
-// entry p >= bn, chosen in turn, gets an empty partial, so that no entry is
-// more than 14 batches old: an entry left from an earlier batch never carries
-// the tag of the batch being read.
+// < bn, an empty one where it had no share), together at the end of the batch,
+// so that no store is in flight while the stripes run (the combine needs every
+// pass anyway). One entry p >= bn, chosen in turn, gets an empty partial, so
+// that no entry is more than 14 batches old: an entry left from an earlier
+// batch never carries the tag of the batch being read.
 template <class PP>
 __device__ __forceinline__ void write_part(const PP& P, int g, uint32_t seq, int p, int c,
                                            const StripeResult& r, uint64_t count) {

@@ -7,12 +7,12 @@
 //
 // What bounds it. Many rows: the matrix cores, and behind them the card's
 // power limit. Under products of random bf16 values the clock falls below
-// 2.0 GHz, so energy per product counts, not only issue slots.
-// v_mfma_f32_16x16x32_bf16 on register operands reaches 1.96-2.11 PFLOP/s
-// where v_mfma_f32_32x32x16_bf16 reaches 1.70-1.83 (same card; its
-// accumulators move twice as often per product), hence 16 x 16 blocks; loads
-// straight into LDS save the passage through registers. Few rows: the one read
-// of the weight from HBM.
+// 2.0 GHz, so energy per product counts, not only issue slots. On register
+// operands of normal values v_mfma_f32_16x16x32_bf16 reaches 2.03 PFLOP/s where
+// v_mfma_f32_32x32x16_bf16 reaches 1.77 (same card; its accumulators move twice
+// as often per product; with zeros or ones both reach 2.42), hence 16 x 16
+// blocks; loads straight into LDS save the passage through registers. Few rows:
+// the one read of the weight from HBM.
 //
 // Tiling. A workgroup of 4 wavefronts (2 x 2, one per SIMD) computes a
 // 32 MB x 256 tile of logits, each wavefront 16 MB x 128 of it as MB x 8
@@ -95,11 +95,12 @@ constexpr int stages(int mb) {
 // Tile i of the launch's order: groups of kGroupN column tiles, in a group row
 // by row. The 32 tiles an XCD runs at once are then four rows by eight columns
 // that share their slices through its L2, and all XCDs read the same eight
-// column tiles of the weight at about the same time, so the weight comes from
-// HBM once and the rest from the last-level cache. (With each XCD on a
-// contiguous eighth of all tiles, the XCDs sat at different columns and each
-// fetched the weight for itself: 13.8 against 12.5 ms at 16640 x 4096 x
-// 128256; groups of 4 or 16 columns 13.1 and 12.2 against 12.1 ms.)
+// column tiles of the weight at about the same time, where the last-level cache
+// can serve all but the first. (With each XCD on a contiguous eighth of all
+// tiles, the XCDs sat at different columns: 13.8 against 12.5 ms at 16640 x
+// 4096 x 128256; groups of 4 or 16 columns 13.1 and 12.2 against 12.1 ms. What
+// leaves the L2s is the same, 32 GB read; no counter here tells the last-level
+// cache's part of it from the memory's.)
 __device__ __forceinline__ void tile_at(const LmParams& P, int i, int& tm, int& tn) {
   const int per = kGroupN * P.tiles_m;
   const int g = i / per, in = i - g * per;
