@@ -573,6 +573,9 @@ def test_masked_vocabulary_and_misaligned_base():
 
 
 def test_deterministic():
+    """64 trees at V = 50000: groups of 12 workgroups, as many as may contribute
+    (no helpers), and nothing else on the device, so every group begins
+    complete and the outputs are the same bit for bit."""
     bt = W.make_batch(5, step=4, device=DEV, mode=W.WITHOUT_REPLACEMENT, batch=64, vocab=50000)
     a = parity.run_gpu(bt, False, p_init=True)
     b = parity.run_gpu(bt, False, p_init=True)
