@@ -2,7 +2,7 @@
 inline assembly that the compiler's hazard recogniser does not look into. The
 wait states that CDNA4 asks for around them are either in that assembly or, for
 the three checked here, come from where the compiler puts its own instructions:
-in this build (44 s to compile) they have to be there on every path."""
+in the code as compiled (44 s) they have to be there on every path."""
 
 import functools
 import os
